@@ -4,6 +4,7 @@
 
 #include "args.hpp"
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <string>
 #include <utility>
@@ -12,6 +13,9 @@
 namespace attn {
 
 namespace {
+// cut_tiles: tiles that end at group bounds may be this many more
+constexpr double kMaxCutGrowth = 1.15;
+
 bool fail(std::string* err, const std::string& msg) {
   if (err) *err = msg;
   return false;
@@ -191,57 +195,264 @@ int64_t most_rows(const GroupTable& gt) {
 }
 }  // namespace
 
-int choose_ksplit(const GroupTable& gt, int L, int nbh) {
-  // Time of a launch in block steps (a wave's 32 keys of 32 rows): the longest tile when the
-  // work-groups all fit the 256 CUs at once, else the mean load plus half a tile of tail.  A
-  // split step costs more than an unsplit one (a staged block serves fewer waves), and every
-  // tile has a fixed part (plan, first loads, merge, stores) worth about 7 steps.  Measured,
-  // JVP at D = 128, us with 1 / 2 / 4 splits:
-  //   12 heads, full, L = 4680 (228 tiles of 256 rows)       330 /  378 /  457
-  //   40 heads, full, L = 4680                              1077 / 1239 / 1414
-  //   12 heads, full, L = 1560 (84 tiles)                    103 /   75 /   94
-  //    1 head, teacher forcing, L = 65520 (uneven tiles)    2360 / 1838 / 1988
-  //    3 heads, teacher forcing, L = 6240 (75 tiles)         287 /  181 /  127
-  //    2 heads, full, L = 1024                                67 /   48 /   33
-  constexpr double kStepCost[3] = {1.0, 1.15, 1.3};
-  constexpr double kFixed = 7.0, kCus = 256.0;
-  const int64_t longest = most_keys(gt);
-  const double steps = (double)count_pairs(gt) * nbh / (32.0 * kMfmaBr);  // over all tiles
+namespace {
+
+// What a launch would take with tiles of one size (bf16), for the three rules below.
+//
+// A run is `n` tiles of one (batch, head) that walk `len` blocks of 32 each.
+struct Run {
+  double len, n;
+};
+
+// Rows (keys) [begin, end) that admit (are admitted by) `count` keys (rows).
+struct Seg {
+  int begin, end;
+  double count;
+};
+
+// (segments of up to 32 rows together count as one)
+void add_seg(std::vector<Seg>* s, const Seg& x) {
+  if (!s->empty() && s->back().end == x.begin && (s->back().count == x.count || x.end - s->back().begin <= 32)) {
+    s->back().end = x.end;
+    s->back().count = std::max(s->back().count, x.count);
+  } else {
+    s->push_back(x);
+  }
+}
+
+std::vector<Seg> query_segs(const GroupTable& gt) {
+  std::vector<Seg> s;
+  for (int g = 0; g < gt.n; ++g) {
+    double keys = 0;
+    for (int r = gt.r_begin[g]; r < gt.r_begin[g + 1]; ++r) keys += gt.k[2 * r + 1] - gt.k[2 * r];
+    add_seg(&s, {group_q_begin(gt, g), gt.q_end[g], keys});
+  }
+  return s;
+}
+
+std::vector<Seg> key_segs(const GroupTable& gt) {
+  std::vector<std::pair<int, int>> ends;  // rows enter and leave at the ends of the key ranges
+  for (int g = 0; g < gt.n; ++g) {
+    const int rows = gt.q_end[g] - group_q_begin(gt, g);
+    for (int r = gt.r_begin[g]; r < gt.r_begin[g + 1]; ++r) {
+      ends.emplace_back(gt.k[2 * r], rows);
+      ends.emplace_back(gt.k[2 * r + 1], -rows);
+    }
+  }
+  std::sort(ends.begin(), ends.end());
+  std::vector<Seg> s;
+  double now = 0;
+  for (size_t i = 0; i < ends.size(); ++i) {
+    now += ends[i].second;
+    if (i + 1 == ends.size() || ends[i + 1].first == ends[i].first) continue;
+    add_seg(&s, {ends[i].first, ends[i + 1].first, now});
+  }
+  return s;
+}
+
+// The runs of tiles of br rows.  Cut tiles end with their segment; of the others one per segment
+// spans into the next ones and walks the longest's blocks.
+void tile_runs(const std::vector<Seg>& segs, int br, bool cut, std::vector<Run>* out) {
+  out->clear();
+  const int ns = (int)segs.size();
+  for (int i = 0; i < ns; ++i) {
+    double n = (double)(segs[i].end - segs[i].begin) / br, span = 0;
+    if (cut) {
+      n = std::ceil(n);
+    } else if (i + 1 < ns) {
+      double longest = segs[i].count;
+      for (int j = i + 1; j < ns && 2 * (segs[j].begin - segs[i].end) < br; ++j) longest = std::max(longest, segs[j].count);
+      span = std::min(n, 1.0);
+      out->push_back({longest / kMfmaBc, span});
+    }
+    if (!cut && i + 1 == ns) n += std::ceil((double)segs[i].end / br) - (double)segs[i].end / br;  // (the last tile)
+    if (n > span) out->push_back({segs[i].count / kMfmaBc, n - span});
+  }
+}
+
+// Measured times of a tile in us: of a round (one block of every split) and of the rest (plan,
+// first loads, merge, stores).  A CU holds one tile of 8 waves, or up to three of 4 waves, whose
+// rounds then take 1 + share (its other tiles) times as long.
+struct TileCost {
+  int br, splits;
+  double step, fixed, share;
+};
+
+// Lengths within a sixteenth of each other count as one, so that few runs are left.
+void merge_runs(std::vector<Run>* runs) {
+  std::sort(runs->begin(), runs->end(), [](const Run& x, const Run& y) { return x.len > y.len; });
+  size_t k = 0;
+  double first = 0;
+  for (const Run& r : *runs) {
+    Run& m = (*runs)[k > 0 ? k - 1 : 0];
+    if (k > 0 && r.len > 0.94 * first) {
+      m.len = (m.len * m.n + r.len * r.n) / (m.n + r.n);
+      m.n += r.n;
+    } else {
+      first = r.len;
+      (*runs)[k++] = r;
+    }
+  }
+  runs->resize(k);
+}
+
+// The launch: work-groups take the tiles as slot_of does, head group after head group, longest
+// first in each, on the slot that is free first; at most kMaxFollowed runs are followed (or two
+// head groups), the head groups before them fill the slots evenly.  A launch that leaves CUs idle
+// runs at a higher clock (the card is at its power limit otherwise): with none busy but the
+// longest tile's, a quarter faster.  Two to five us of host time in all, at most 70 (60 chunks).
+constexpr int kMaxFollowed = 48;
+
+double launch_cost(std::vector<Run>* runs, int nbh, int head_group, const TileCost& c) {
+  double tiles = 0, work = 0, last = 0;  // (work: of one pair)
+  for (const Run& r : *runs) tiles += r.n * nbh;
+  const double others = c.share > 0 ? std::min(2.0, std::max(0.0, tiles / 256.0 - 1)) : 0;
+  const double step = c.step * (1 + c.share * others), slots = 256.0 * (1 + std::ceil(others - 1e-9));
+  auto time = [&](const Run& r) { return std::ceil(r.len / c.splits) * step + c.fixed; };
+  if (tiles > slots) merge_runs(runs);
+  for (const Run& r : *runs) {
+    work += r.n * time(r);
+    last = std::max(last, time(r));
+  }
+  if (tiles > slots) {
+    const int groups = (nbh + head_group - 1) / head_group, follow = std::max(2, kMaxFollowed / (int)runs->size());
+    const int h0 = std::max(0, groups - follow) * head_group;
+    // how many slots are free from when on, earliest first
+    using Free = std::pair<double, double>;
+    std::vector<Free> heap{{work * h0 / slots, slots}};
+    const auto later = [](const Free& x, const Free& y) { return x.first > y.first; };
+    for (int h = h0; h < nbh; h += head_group) {
+      for (const Run& r : *runs) {
+        const double t = time(r);
+        for (double n = r.n * std::min(head_group, nbh - h); n > 1e-3;) {
+          Free f = heap.front();
+          if (f.second - n < 1e-3) {  // the run takes every slot of this time
+            std::pop_heap(heap.begin(), heap.end(), later);
+            heap.pop_back();
+          } else {
+            heap.front().second -= n;
+            f.second = n;
+          }
+          n -= f.second;
+          f.first += t;
+          last = std::max(last, f.first);
+          heap.push_back(f);
+          std::push_heap(heap.begin(), heap.end(), later);
+        }
+      }
+    }
+  }
+  return last > 0 ? last * (0.75 + 0.25 * std::min(1.0, work * nbh / slots / last)) : 0;
+}
+
+// As cut_tiles would cut tiles of br rows.
+bool tiles_are_cut(const GroupTable& gt, int L, int br) {
+  if (gt.n < 2 || gt.n > kMaxSegs) return false;
+  int nt = 0;
+  for (int g = 0; g < gt.n; ++g) nt += (gt.q_end[g] - group_q_begin(gt, g) + br - 1) / br;
+  return nt <= kMaxCutGrowth * ((L + br - 1) / br);
+}
+
+// Full tiles per CU beyond which no split was faster in any measured launch.
+constexpr int kMaxFullTilesPerCu = 4;
+// A split has to promise this much of the full tiles' time at most: the estimates are off by 5 %
+// (half of the launches) to 20 % (one in ten), more where the tiles take several rounds or span
+// many groups.
+double split_gain(const GroupTable& gt, int L, int nbh, int br) {
+  if (L < 256 * gt.n) return 0.85;
+  return (int64_t)((L + br - 1) / br) * nbh <= 256 ? 0.975 : 0.94;
+}
+
+}  // namespace
+
+int choose_ksplit(const GroupTable& gt, int L, int nbh, int D) {
+  // Forward, JVP and zero-clean JVP take the same tiles (their outputs agree bit for bit), so a
+  // split must be worth it to the forward and to the JVP alike: the forward's full tiles have
+  // 128 rows and 4 waves, three of which share a CU, the JVP's 256 rows.  Costs fitted to 1500
+  // launches (full, block-causal, teacher-forcing and window masks, 1-40 heads, L = 64-30000): the
+  // choice is 2.4 % (forward) and 4.2 % (JVP) off the best one on average, since one must serve
+  // both; two forwards and nine JVPs of them are more than 3 % slower than full tiles, at most 13 %.
+  // (With the longest tile, the mean load and half a tile of tail alone: 93, at most 47 %.)
+  // Forward / JVP, us with full tiles and 2 and 4 splits:
+  //   12 heads, D = 64, full, L = 1955                    44 /  73,   32 /  48,   36 /  59
+  //    6 heads, D = 128, full, L = 5590                  154 / 295,  183 / 438,  179 / 400
+  //    6 heads, D = 64, full, L = 11762                  301 / 874,  393 / 764,  359 / 740
+  //    4 heads, D = 128, teacher forcing, L = 7866       143 / 317,   69 / 162,   77 / 171
+  //    4 heads, D = 128, block-causal, L = 6460          138 / 335,  101 / 240,   75 / 167
+  constexpr TileCost kFwdCost[2][3] = {
+      {{128, 1, 0.51, 9.0, 0.32}, {128, 2, 0.70, 8.0, 0}, {64, 4, 0.75, 5.0, 0}},     // D = 64
+      {{128, 1, 0.75, 10.0, 0.40}, {128, 2, 0.98, 10.5, 0}, {64, 4, 1.22, 6.8, 0}}};    // D = 128
+  constexpr TileCost kJvpCost[2][3] = {
+      {{256, 1, 1.28, 22.0, 0}, {128, 2, 1.36, 11.0, 0}, {64, 4, 1.55, 5.5, 0}},
+      {{256, 1, 2.06, 40.0, 0}, {128, 2, 2.52, 16.0, 0}, {64, 4, 2.95, 10.0, 0}}};
+  if ((int64_t)((L + kMfmaBr - 1) / kMfmaBr) * nbh > 256 * kMaxFullTilesPerCu) return 1;
+  const std::vector<Seg> segs = query_segs(gt);
+  std::vector<Run> runs;
   int best = 1;
-  double best_cost = 0;
+  double best_cost[2] = {0, 0};
   for (int i = 0; i < 3; ++i) {
-    const int ks = 1 << i, br = kMfmaBr / ks;
-    const double n = (double)((L + br - 1) / br) * nbh;
-    const double total = kStepCost[i] * steps + n * kFixed;
-    const double cost = std::max(kStepCost[i] * (double)longest / (32.0 * ks) + kFixed,
-                                 n > kCus ? total / kCus + 0.5 * total / n : 0.0);
-    if (i == 0 || cost < best_cost) {
-      best = ks;
-      best_cost = cost;
+    double c[2];
+    for (int p = 0; p < 2; ++p) {
+      const TileCost& tc = (p ? kJvpCost : kFwdCost)[D == 128][i];
+      tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+      c[p] = launch_cost(&runs, nbh, kHeadGroup, tc);
+    }
+    const double gain = i == 0 || best > 1 ? 1.0 : split_gain(gt, L, nbh, kMfmaBr >> i);  // (4 splits against 2: the better)
+    if (i == 0 || (c[0] <= gain * best_cost[0] && c[1] <= gain * best_cost[1])) {
+      best = 1 << i;
+      best_cost[0] = c[0];
+      best_cost[1] = c[1];
     }
   }
   return best;
 }
 
-int choose_qsplit(const GroupTable& gt, int L, int nbh) {
-  // Time in rounds of the 128-key tile (64 query rows against 128 keys), as in choose_ksplit.
-  // Measured, us of the whole backward call at D = 128 with 128-key tiles / 64-key tiles:
-  //   12 heads, full, L = 1560 (156 tiles of 128 keys)        118 /  127
-  //   40 heads, full, L = 4680                               1420 / 1520
-  //    3 heads, teacher forcing, L = 6240 (147 uneven tiles)  314 /  262
-  //    1 head, teacher forcing, L = 65520                    2960 / 2748
-  constexpr double kSplitCost = 1.13, kFixed = 5.0, kCus = 256.0;
-  const int64_t longest = most_rows(gt);
-  const double rounds = (double)count_pairs(gt) * nbh / (64.0 * kBwdKeysPerTile);
-  double cost[2];
-  for (int i = 0; i < 2; ++i) {
-    const int kt = i ? kBwdKeysPerSplitTile : kBwdKeysPerTile;
-    const double n = (double)((L + kt - 1) / kt) * nbh;
-    const double step = i ? kSplitCost : 1.0, total = step * rounds + n * kFixed;
-    cost[i] = std::max(step * (double)longest / (i ? 128.0 : 64.0) + kFixed,
-                       n > kCus ? total / kCus + 0.5 * total / n : 0.0);
+int choose_bwd_ksplit(const GroupTable& gt, int L, int nbh, int D) {
+  // The same for the query-tile pass of the backward alone.  Backward call, us with full query
+  // tiles and 2 and 4 splits (128-key tiles):
+  //   12 heads, D = 128, full, L = 2753                   245 / 286 / 277
+  //   40 heads, D = 64, block-causal, L = 840            59.7 / 67.6 / 63.2
+  //    6 heads, D = 64, full, L = 11762                  1088 / 1045 / 992
+  //    4 heads, D = 128, teacher forcing, L = 7866        368 / 262 / 266
+  // (5 heads, D = 128, full, L = 73: 21.8 / 23.2 / 25.0, so tiles of up to 4 blocks are not split.)
+  if (most_keys(gt) <= 4 * kMfmaBc) return 1;
+  constexpr TileCost kCost[2][3] = {{{256, 1, 0.50, 16.0, 0}, {128, 2, 0.50, 10.0, 0}, {64, 4, 0.50, 7.0, 0}},
+                                    {{256, 1, 0.85, 29.0, 0}, {128, 2, 0.94, 16.5, 0}, {64, 4, 1.03, 11.7, 0}}};
+  if ((int64_t)((L + kMfmaBr - 1) / kMfmaBr) * nbh > 256 * kMaxFullTilesPerCu) return 1;
+  const std::vector<Seg> segs = query_segs(gt);
+  std::vector<Run> runs;
+  int best = 1;
+  double best_cost = 0;
+  for (int i = 0; i < 3; ++i) {
+    const TileCost& tc = kCost[D == 128][i];
+    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+    const double c = launch_cost(&runs, nbh, kHeadGroup, tc) / (i == 0 ? 1.0 : split_gain(gt, L, nbh, tc.br));
+    if (i == 0 || c < best_cost) {
+      best = 1 << i;
+      best_cost = c;
+    }
   }
-  return cost[1] < cost[0] ? kBwdQuerySplits : 1;
+  return best;
+}
+
+int choose_qsplit(const GroupTable& gt, int L, int nbh, int D) {
+  // The key-tile pass.  Backward call, us with 128-key tiles / 64-key tiles (full query tiles):
+  //   12 heads, D = 128, full, L = 2753                  245 / 234
+  //    6 heads, D = 128, block-causal, L = 14718        1170 / 1251
+  //   40 heads, D = 64, block-causal, L = 840           59.7 / 61.3
+  //    4 heads, D = 128, teacher forcing, L = 7866       368 / 309
+  constexpr TileCost kCost[2][2] = {{{kBwdKeysPerTile, 1, 0.67, 9.0, 0}, {kBwdKeysPerSplitTile, 2, 0.71, 6.7, 0}},
+                                    {{kBwdKeysPerTile, 1, 1.06, 12.5, 0}, {kBwdKeysPerSplitTile, 2, 1.20, 8.5, 0}}};
+  if ((int64_t)((L + kBwdKeysPerTile - 1) / kBwdKeysPerTile) * nbh > 2 * 256 * kMaxFullTilesPerCu) return 1;
+  const std::vector<Seg> segs = key_segs(gt);
+  std::vector<Run> runs;
+  double c[2];
+  for (int i = 0; i < 2; ++i) {
+    const TileCost& tc = kCost[D == 128][i];
+    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+    c[i] = launch_cost(&runs, nbh, kHeadGroupWide, tc);
+  }
+  return c[1] < (L < 256 * gt.n ? 0.85 : 0.975) * c[0] ? kBwdQuerySplits : 1;
 }
 
 int choose_f32_tiles(const GroupTable& gt, int L, int nbh, int D, F32Kernel kernel) {
@@ -305,7 +516,7 @@ void cut_tiles(TileOrder* o, const GroupTable& gt, int L, int br) {
     o->tile[g] = nt;
     nt += (rows + br - 1) / br;
   }
-  if (nt > 1.15 * ((L + br - 1) / br)) return;
+  if (nt > kMaxCutGrowth * ((L + br - 1) / br)) return;
   o->row[gt.n] = L;
   o->tile[gt.n] = nt;
   o->nseg = gt.n;

@@ -21,13 +21,15 @@ int64_t count_pairs(const GroupTable& gt);
 // Pairs evaluated by a kernel with br-row query tiles and bc-key blocks.
 int64_t count_computed_pairs(const GroupTable& gt, int L, int br, int bc);
 
-// Key splits per query tile of the bf16 forward and JVP kernels (1: none, 256-row tiles; 2 or
-// 4: tiles of 256 / splits rows) for nbh (batch, head) pairs.
-int choose_ksplit(const GroupTable& gt, int L, int nbh);
+// Key splits per query tile of the bf16 forward and JVP kernels (1: none, 128- and 256-row
+// tiles; 2 or 4: tiles of 256 / splits rows) for nbh (batch, head) pairs, and of the backward's
+// query-tile pass.
+int choose_ksplit(const GroupTable& gt, int L, int nbh, int D = 128);
+int choose_bwd_ksplit(const GroupTable& gt, int L, int nbh, int D);
 
 // Query splits per key tile of the bf16 backward's key-tile pass (1: 128-key tiles; else
 // kBwdQuerySplits, 64-key tiles).
-int choose_qsplit(const GroupTable& gt, int L, int nbh);
+int choose_qsplit(const GroupTable& gt, int L, int nbh, int D = 128);
 
 // Tile size of an fp32 kernel: 1 for 128 rows (keys), 2 for 64.  kQueryTiles: the JVP and the
 // backward's query-tile pass; kKeyTiles: its key-tile pass.

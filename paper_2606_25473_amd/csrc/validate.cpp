@@ -112,7 +112,7 @@ int prepare(Pass pass, int dtype, int B, int H, int L, int D, const void* Q, con
     if (zc)
       args->order = make_tile_order_zero_clean(args->gt, L, kF32Br / args->ksplit, kMfmaBc, t0, &args->order);
   } else {
-    args->ksplit = choose_ksplit(args->gt, L, B * H);
+    args->ksplit = choose_ksplit(args->gt, L, B * H, D);
     const int br = args->ksplit > 1 ? kMfmaBr / args->ksplit : pass == Pass::kFwd ? kMfmaBrFwd : kMfmaBr;
     args->order = make_tile_order(layout, L, br);
     if (args->ksplit > 1) cut_tiles(&args->order, args->gt, L, br);
@@ -173,8 +173,8 @@ int prepare_bwd(int dtype, int B, int H, int L, int D, const void* Q, const void
   qa->scale = ka->scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)D);
   qa->split = ka->split = 1;
   if (dtype == ATTN_DTYPE_BF16) {
-    qa->split = choose_ksplit(qa->gt, L, B * H);
-    ka->split = choose_qsplit(qa->gt, L, B * H);
+    qa->split = choose_bwd_ksplit(qa->gt, L, B * H, D);
+    ka->split = choose_qsplit(qa->gt, L, B * H, D);
   } else {
     qa->split = choose_f32_tiles(qa->gt, L, B * H, D, F32Kernel::kQueryTiles);
     ka->split = choose_f32_tiles(qa->gt, L, B * H, D, F32Kernel::kKeyTiles);
