@@ -23,8 +23,9 @@ struct Span {
 bool overlap(const Span& x, const Span& y) { return x.lo < y.hi && y.lo < x.hi; }
 
 // Size limits of the kernels (after the positivity checks): the kernels address a head with
-// 32-bit byte offsets and launch one work-group per tile of at least 128 rows or keys and
-// (batch, head), in one grid dimension.
+// 32-bit byte offsets and launch one work-group per tile and (batch, head), in one grid
+// dimension.  The limit counts uncut tiles of 128 rows; smaller and cut tiles are only taken
+// where they fit the grid too (the rules of layout.hpp, cut_within_grid).
 int check_sizes(int dtype, int B, int H, int L, int D) {
   const int64_t bh = (int64_t)B * H;
   if (bh > (int64_t)1 << 20) return fail(ATTN_ERR_INVALID, "B * H too large");
@@ -37,6 +38,13 @@ int check_sizes(int dtype, int B, int H, int L, int D) {
   if (((int64_t)L + 127) / 128 * bh > INT32_MAX)
     return fail(ATTN_ERR_INVALID, "too many work-groups for one launch: ceil(L / 128) * B * H > 2^31 - 1");
   return ATTN_OK;
+}
+
+// cut_tiles, unless the launch would then have more work-groups than a grid holds
+void cut_within_grid(TileOrder* o, const GroupTable& gt, int L, int br, int nbh) {
+  TileOrder cut = *o;
+  cut_tiles(&cut, gt, L, br);
+  if ((int64_t)cut.nt * nbh <= INT32_MAX) *o = cut;
 }
 
 int elem_size(int dtype) { return dtype == ATTN_DTYPE_F32 ? 4 : dtype == ATTN_DTYPE_BF16 ? 2 : 0; }
@@ -108,14 +116,14 @@ int prepare(Pass pass, int dtype, int B, int H, int L, int D, const void* Q, con
   if (dtype == ATTN_DTYPE_F32) {
     args->ksplit = choose_f32_tiles(args->gt, L, B * H, D, jvp ? F32Kernel::kQueryTiles : F32Kernel::kForward);
     args->order = make_tile_order(layout, L, kF32Br / args->ksplit);
-    cut_tiles(&args->order, args->gt, L, kF32Br / args->ksplit);
+    cut_within_grid(&args->order, args->gt, L, kF32Br / args->ksplit, B * H);
     if (zc)
       args->order = make_tile_order_zero_clean(args->gt, L, kF32Br / args->ksplit, kMfmaBc, t0, &args->order);
   } else {
     args->ksplit = choose_ksplit(args->gt, L, B * H, D);
     const int br = args->ksplit > 1 ? kMfmaBr / args->ksplit : pass == Pass::kFwd ? kMfmaBrFwd : kMfmaBr;
     args->order = make_tile_order(layout, L, br);
-    if (args->ksplit > 1) cut_tiles(&args->order, args->gt, L, br);
+    if (args->ksplit > 1) cut_within_grid(&args->order, args->gt, L, br, B * H);
     if (zc) args->order = make_tile_order_zero_clean(args->gt, L, br, kMfmaBc, t0, &args->order);
   }
   return ATTN_OK;
@@ -181,7 +189,7 @@ int prepare_bwd(int dtype, int B, int H, int L, int D, const void* Q, const void
   }
   const int br = (dtype == ATTN_DTYPE_F32 ? kF32Br : kMfmaBr) / qa->split;
   qa->order = make_tile_order(layout, L, br);
-  if (dtype == ATTN_DTYPE_F32 || qa->split > 1) cut_tiles(&qa->order, qa->gt, L, br);
+  if (dtype == ATTN_DTYPE_F32 || qa->split > 1) cut_within_grid(&qa->order, qa->gt, L, br, B * H);
   // key tiles: for the built-in layouts the work per key tile falls with the key index
   // (earlier keys are seen by more queries), so the natural order is heaviest first
   ka->order = TileOrder{};
@@ -191,7 +199,7 @@ int prepare_bwd(int dtype, int B, int H, int L, int D, const void* Q, const void
   ka->order.split = ka->order.nt;
   ka->order.first = -1;
   // (the built-in layouts' key ranges end at the query groups' bounds)
-  if (dtype == ATTN_DTYPE_F32 || ka->split > 1) cut_tiles(&ka->order, ka->gt, L, kt);
+  if (dtype == ATTN_DTYPE_F32 || ka->split > 1) cut_within_grid(&ka->order, ka->gt, L, kt, B * H);
   return ATTN_OK;
 }
 

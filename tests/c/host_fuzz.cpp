@@ -312,6 +312,30 @@ int main(int argc, char** argv) {
     r.ranges.resize(2 * ATTN_MAX_RANGES);
     check_layout(r);
   }
+  // the largest launches: 2^20 heads of 2047 tiles, whose cut tiles a grid no longer holds
+  {
+    const int B = 1024, H = 1024, L = 2047 * 128;
+    const int32_t offs[4] = {0, 40 * 128 + 1, 900 * 128 + 7, L};
+    const int32_t half[3] = {0, 33, L / 2};
+    const attn_chunk_layout bc = {ATTN_MASK_BLOCK_CAUSAL, 3, offs, nullptr, nullptr};
+    const attn_chunk_layout tf = {ATTN_MASK_TEACHER_FORCING, 2, half, nullptr, nullptr};
+    auto ptr = [](int i) { return (void*)((uintptr_t)(i + 1) << 50); };
+    for (int dtype : {ATTN_DTYPE_F32, ATTN_DTYPE_BF16})
+      for (const attn_chunk_layout* lay : {&bc, &tf}) {
+        for (attn::Pass pass : {attn::Pass::kFwd, attn::Pass::kJvp, attn::Pass::kJvpZeroClean}) {
+          if (pass == attn::Pass::kJvpZeroClean && lay != &tf) continue;
+          attn::AttnArgs a;
+          CHECK(attn::prepare(pass, dtype, B, H, L, 64, ptr(0), ptr(1), ptr(2), ptr(3), ptr(4), ptr(5), lay, 0.f, ptr(6),
+                              ptr(7), (float*)ptr(8), &a) == ATTN_OK, "largest launch refused: %s", attn::last_error_message());
+          CHECK((int64_t)a.order.nt * B * H <= INT32_MAX, "%d tiles of 2^20 heads", a.order.nt);
+        }
+        attn::BwdArgs qa, ka;
+        CHECK(attn::prepare_bwd(dtype, B, H, L, 64, ptr(0), ptr(1), ptr(2), ptr(3), ptr(4), (const float*)ptr(5), lay, 0.f,
+                                ptr(6), ptr(7), ptr(8), (float*)ptr(9), &qa, &ka) == ATTN_OK, "largest backward refused");
+        CHECK((int64_t)qa.order.nt * B * H <= INT32_MAX && (int64_t)ka.order.nt * B * H <= INT32_MAX,
+              "%d and %d tiles of 2^20 heads", qa.order.nt, ka.order.nt);
+      }
+  }
   std::printf(fails ? "FAIL %d\n" : "OK\n", fails);
   return fails ? 1 : 0;
 }
