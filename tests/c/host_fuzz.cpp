@@ -1,7 +1,7 @@
 // Seeded fuzz of the library's host code, built with g++ -fsanitize=address,undefined
 // (tests/test_host_sanitized.py): layout validation and the query-group table, pair
 // counts, the query-tile and key-tile plans and their per-row / per-key mask bits (also
-// for windows past the end of the sequence), the tile orders, and the argument
+// for windows past the end of the sequence), the tile orders, cuts and rules, and the argument
 // validation of every compute entry point with fake, never dereferenced pointers.
 // Every derived quantity is checked against a brute-force mask taken from the layout's
 // own definition (chunk ids, or the caller's raw range arrays), not from the table.
@@ -204,6 +204,44 @@ void check_layout(const Layout& l) {
   CHECK(perm(attn::make_tile_order(&c, L, attn::kMfmaBrFwd)), "forward tile order");
   if (l.kind == ATTN_MASK_TEACHER_FORCING)
     CHECK(perm(attn::make_tile_order_zero_clean(gt, L, attn::kMfmaBr, attn::kMfmaBc, L / 2)), "zero-clean order");
+  // tiles cut at group bounds: every row in one tile, in order, no tile over a bound; their
+  // orders are permutations, the zero-clean one of tiles wholly on one side of L / 2
+  for (int br : {64, 128}) {
+    attn::TileOrder cut = attn::make_tile_order(&c, L, br);
+    const int uncut = cut.nt;
+    attn::cut_tiles(&cut, gt, L, br);
+    CHECK(cut.nseg > 0 || cut.nt == uncut, "tile count changed without cuts");
+    std::vector<attn::TileOrder> orders{cut};
+    if (l.kind == ATTN_MASK_TEACHER_FORCING) {
+      orders.push_back(attn::make_tile_order_zero_clean(gt, L, br, attn::kMfmaBc, L / 2, &cut));
+      orders.push_back(attn::make_tile_order_zero_clean(gt, L, br, attn::kMfmaBc, L / 2));
+    }
+    for (const attn::TileOrder& o : orders) {
+      CHECK(perm(o), "order of cut tiles");
+      int at = 0;
+      for (int t = 0; t < o.nt; ++t) {
+        int a, b;
+        attn::tile_rows(o, t, br, L, &a, &b);
+        CHECK(a == at && b > a && b <= a + br, "rows [%d, %d) of tile %d", a, b, t);
+        if (o.nseg > 0) CHECK(attn::find_group(gt, a) == attn::find_group(gt, b - 1), "tile %d spans a bound", t);
+        at = b;
+      }
+      CHECK(at == L, "tiles end at %d of %d", at, L);
+    }
+  }
+  // the tile rules
+  for (int nbh : {1, 7, 40, 1 << 20})
+    for (int D : {64, 128}) {
+      const int ks = attn::choose_ksplit(gt, L, nbh, D), bs = attn::choose_bwd_ksplit(gt, L, nbh, D);
+      const int qs = attn::choose_qsplit(gt, L, nbh, D);
+      CHECK((ks == 1 || ks == 2 || ks == 4) && (bs == 1 || bs == 2 || bs == 4) && (qs == 1 || qs == attn::kBwdQuerySplits),
+            "splits %d %d %d", ks, bs, qs);
+      if (nbh == 1 << 20) CHECK(ks == 1 && bs == 1 && qs == 1, "split tiles in a launch that fills the chip");
+      for (auto k : {attn::F32Kernel::kForward, attn::F32Kernel::kQueryTiles, attn::F32Kernel::kKeyTiles}) {
+        const int f = attn::choose_f32_tiles(gt, L, nbh, D, k);
+        CHECK(f == 1 || f == 2, "fp32 tiles %d", f);
+      }
+    }
   // the host entry points on this layout
   std::vector<int32_t> bounds(ATTN_MAX_GROUPS + 1), ro(ATTN_MAX_GROUPS + 1), rk(2 * ATTN_MAX_RANGES);
   CHECK(attn_query_groups(&c, L, bounds.data(), ro.data(), rk.data(), ATTN_MAX_GROUPS, ATTN_MAX_RANGES) == gt.n,
