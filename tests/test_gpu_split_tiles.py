@@ -149,10 +149,10 @@ F32 = [custom_workload(f"f32_{kind}_{L}_{D}", 1, H, D, "f32", kind, L=L if kind 
 @pytest.mark.parametrize("w", F32, ids=lambda w: f"{w.name}_H{w.H}")
 def test_f32_three_part_products(w):
     """fp32 by bf16 part products, 64- and 128-row tiles: relative L2 <= 2e-6 against the oracle.
-    Per product the parts left out are below 2^-25 and an element takes at most L / 32 + 8
-    roundings of 2^-24 at the size of its result, random in sign: sqrt(40) 2^-24 = 4e-7, and as
-    much again for exp2 and the scores (measured 2e-7 to 6e-7); a dropped part would show as
-    2^-17."""
+    Per product the parts left out are below 2^-24 (0.09 2^-24 rms, either sign) and an element
+    takes at most L / 32 + 8 roundings of 2^-24 at the size of its result, random in sign:
+    sqrt(40) 2^-24 = 4e-7, and as much again for exp2 and the scores (measured 2e-7 to 6e-7); a
+    dropped part would show as 2^-17."""
     offs = list(w.offsets) or None
     x = make_inputs(w, "cpu", 4)
     g, n = {k: v.cuda() for k, v in x.items()}, {k: _np(v) for k, v in x.items()}
