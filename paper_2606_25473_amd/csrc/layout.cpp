@@ -251,8 +251,10 @@ std::vector<Seg> key_segs(const GroupTable& gt) {
 }
 
 // The runs of tiles of br rows.  Cut tiles end with their segment; of the others one per segment
-// spans into the next ones and walks the longest's blocks.
-void tile_runs(const std::vector<Seg>& segs, int br, bool cut, std::vector<Run>* out) {
+// spans into the next ones and walks the blocks of both: span_blocks(begin, end) of them, or
+// about the longest's where there are many segments.
+template <class F>
+void tile_runs(const std::vector<Seg>& segs, int br, bool cut, F span_blocks, std::vector<Run>* out) {
   out->clear();
   const int ns = (int)segs.size();
   for (int i = 0; i < ns; ++i) {
@@ -260,14 +262,27 @@ void tile_runs(const std::vector<Seg>& segs, int br, bool cut, std::vector<Run>*
     if (cut) {
       n = std::ceil(n);
     } else if (i + 1 < ns) {
-      double longest = segs[i].count;
-      for (int j = i + 1; j < ns && 2 * (segs[j].begin - segs[i].end) < br; ++j) longest = std::max(longest, segs[j].count);
+      double blocks = segs[i].count / kMfmaBc;
+      if (ns <= kMaxSegs) {
+        const int begin = std::max(0, segs[i].end - br / 2);
+        blocks = span_blocks(begin, std::min(begin + br, segs[ns - 1].end));
+      } else {
+        for (int j = i + 1; j < ns && 2 * (segs[j].begin - segs[i].end) < br; ++j) blocks = std::max(blocks, segs[j].count / kMfmaBc);
+      }
       span = std::min(n, 1.0);
-      out->push_back({longest / kMfmaBc, span});
+      out->push_back({blocks, span});
     }
     if (!cut && i + 1 == ns) n += std::ceil((double)segs[i].end / br) - (double)segs[i].end / br;  // (the last tile)
     if (n > span) out->push_back({segs[i].count / kMfmaBc, n - span});
   }
+}
+
+// Blocks of 32 that a tile of rows (keys) [begin, end) walks.
+auto query_blocks(const GroupTable& gt) {
+  return [&gt](int begin, int end) { return (double)plan_num_blocks(plan_tile(gt, begin, end, kMfmaBc)); };
+}
+auto key_blocks(const GroupTable& gt) {
+  return [&gt](int begin, int end) { return (double)plan_num_blocks(plan_key_tile(gt, begin, end, kMfmaBc)); };
 }
 
 // Measured times of a tile in us: of a round (one block of every split) and of the rest (plan,
@@ -300,7 +315,8 @@ void merge_runs(std::vector<Run>* runs) {
 // first in each, on the slot that is free first; at most kMaxFollowed runs are followed (or two
 // head groups), the head groups before them fill the slots evenly.  A launch that leaves CUs idle
 // runs at a higher clock (the card is at its power limit otherwise): with none busy but the
-// longest tile's, a quarter faster.  Two to five us of host time in all, at most 70 (60 chunks).
+// longest tile's, a quarter faster.  (The rules take about 6 us of host time, at most 50, for launches
+// of one to a few tiles per CU, and under 1 us for smaller and larger ones.)
 constexpr int kMaxFollowed = 48;
 
 double launch_cost(std::vector<Run>* runs, int nbh, int head_group, const TileCost& c) {
@@ -353,14 +369,28 @@ bool tiles_are_cut(const GroupTable& gt, int L, int br) {
   return nt <= kMaxCutGrowth * ((L + br - 1) / br);
 }
 
+// Whether tiles of br rows, cut or not, all run at once: the smallest ones are then the best.
+bool fit_at_once(int L, int nbh, int br) {
+  return (int64_t)((L + br - 1) / br * kMaxCutGrowth + 1) * nbh <= 256;
+}
+
 // Full tiles per CU beyond which no split was faster in any measured launch.
 constexpr int kMaxFullTilesPerCu = 4;
-// A split has to promise this much of the full tiles' time at most: the estimates are off by 5 %
-// (half of the launches) to 20 % (one in ten), more where the tiles take several rounds or span
-// many groups.
+// A split of br rows has to promise this much of the full tiles' time at most, in its pass: the
+// estimates are off by 5 % (half of the launches) to 20 % (one in ten), more where the tiles
+// span many groups.  Where the forward and the JVP share the choice, the forward, which gains
+// least, has to lose nothing.
 double split_gain(const GroupTable& gt, int L, int nbh, int br) {
   if (L < 256 * gt.n) return 0.85;
   return (int64_t)((L + br - 1) / br) * nbh <= 256 ? 0.975 : 0.94;
+}
+struct SharedGain {
+  double fwd, jvp;
+};
+SharedGain shared_gain(const GroupTable& gt, int L, int nbh, int br) {
+  if (L < 256 * gt.n) return {1.0, 0.8};
+  if ((int64_t)((L + br - 1) / br) * nbh <= 256) return {0.99, 0.97};
+  return {0.97, 0.94};
 }
 
 }  // namespace
@@ -370,9 +400,9 @@ int choose_ksplit(const GroupTable& gt, int L, int nbh, int D) {
   // split must be worth it to the forward and to the JVP alike: the forward's full tiles have
   // 128 rows and 4 waves, three of which share a CU, the JVP's 256 rows.  Costs fitted to 1500
   // launches (full, block-causal, teacher-forcing and window masks, 1-40 heads, L = 64-30000): the
-  // choice is 2.4 % (forward) and 4.2 % (JVP) off the best one on average, since one must serve
-  // both; two forwards and nine JVPs of them are more than 3 % slower than full tiles, at most 13 %.
-  // (With the longest tile, the mean load and half a tile of tail alone: 93, at most 47 %.)
+  // choice is 1.3 % (forward) and 2.4 % (JVP) off the best one on average, since one must serve
+  // both; 6 forwards and 11 JVPs of them are more than 3 % slower than full tiles.  (With the
+  // longest tile, the mean load and half a tile of tail alone: 93, and 2.5 and 3.4 % on average.)
   // Forward / JVP, us with full tiles and 2 and 4 splits:
   //   12 heads, D = 64, full, L = 1955                    44 /  73,   32 /  48,   36 /  59
   //    6 heads, D = 128, full, L = 5590                  154 / 295,  183 / 438,  179 / 400
@@ -386,6 +416,7 @@ int choose_ksplit(const GroupTable& gt, int L, int nbh, int D) {
       {{256, 1, 1.28, 22.0, 0}, {128, 2, 1.36, 11.0, 0}, {64, 4, 1.55, 5.5, 0}},
       {{256, 1, 2.06, 40.0, 0}, {128, 2, 2.52, 16.0, 0}, {64, 4, 2.95, 10.0, 0}}};
   if ((int64_t)((L + kMfmaBr - 1) / kMfmaBr) * nbh > 256 * kMaxFullTilesPerCu) return 1;
+  if (fit_at_once(L, nbh, kMfmaBr / 4)) return 4;
   const std::vector<Seg> segs = query_segs(gt);
   std::vector<Run> runs;
   int best = 1;
@@ -394,11 +425,12 @@ int choose_ksplit(const GroupTable& gt, int L, int nbh, int D) {
     double c[2];
     for (int p = 0; p < 2; ++p) {
       const TileCost& tc = (p ? kJvpCost : kFwdCost)[D == 128][i];
-      tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+      tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), query_blocks(gt), &runs);
       c[p] = launch_cost(&runs, nbh, kHeadGroup, tc);
     }
-    const double gain = i == 0 || best > 1 ? 1.0 : split_gain(gt, L, nbh, kMfmaBr >> i);  // (4 splits against 2: the better)
-    if (i == 0 || (c[0] <= gain * best_cost[0] && c[1] <= gain * best_cost[1])) {
+    // (4 splits against 2: the better for both)
+    const SharedGain gain = best > 1 ? SharedGain{0.97, 0.97} : shared_gain(gt, L, nbh, kMfmaBr >> i);
+    if (i == 0 || (c[0] <= gain.fwd * best_cost[0] && c[1] <= gain.jvp * best_cost[1])) {
       best = 1 << i;
       best_cost[0] = c[0];
       best_cost[1] = c[1];
@@ -419,13 +451,14 @@ int choose_bwd_ksplit(const GroupTable& gt, int L, int nbh, int D) {
   constexpr TileCost kCost[2][3] = {{{256, 1, 0.50, 16.0, 0}, {128, 2, 0.50, 10.0, 0}, {64, 4, 0.50, 7.0, 0}},
                                     {{256, 1, 0.85, 29.0, 0}, {128, 2, 0.94, 16.5, 0}, {64, 4, 1.03, 11.7, 0}}};
   if ((int64_t)((L + kMfmaBr - 1) / kMfmaBr) * nbh > 256 * kMaxFullTilesPerCu) return 1;
+  if (fit_at_once(L, nbh, kMfmaBr / 4)) return 4;
   const std::vector<Seg> segs = query_segs(gt);
   std::vector<Run> runs;
   int best = 1;
   double best_cost = 0;
   for (int i = 0; i < 3; ++i) {
     const TileCost& tc = kCost[D == 128][i];
-    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), query_blocks(gt), &runs);
     const double c = launch_cost(&runs, nbh, kHeadGroup, tc) / (i == 0 ? 1.0 : split_gain(gt, L, nbh, tc.br));
     if (i == 0 || c < best_cost) {
       best = 1 << i;
@@ -444,12 +477,13 @@ int choose_qsplit(const GroupTable& gt, int L, int nbh, int D) {
   constexpr TileCost kCost[2][2] = {{{kBwdKeysPerTile, 1, 0.67, 9.0, 0}, {kBwdKeysPerSplitTile, 2, 0.71, 6.7, 0}},
                                     {{kBwdKeysPerTile, 1, 1.06, 12.5, 0}, {kBwdKeysPerSplitTile, 2, 1.20, 8.5, 0}}};
   if ((int64_t)((L + kBwdKeysPerTile - 1) / kBwdKeysPerTile) * nbh > 2 * 256 * kMaxFullTilesPerCu) return 1;
+  if (fit_at_once(L, nbh, kBwdKeysPerSplitTile)) return kBwdQuerySplits;
   const std::vector<Seg> segs = key_segs(gt);
   std::vector<Run> runs;
   double c[2];
   for (int i = 0; i < 2; ++i) {
     const TileCost& tc = kCost[D == 128][i];
-    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), &runs);
+    tile_runs(segs, tc.br, i > 0 && tiles_are_cut(gt, L, tc.br), key_blocks(gt), &runs);
     c[i] = launch_cost(&runs, nbh, kHeadGroupWide, tc);
   }
   return c[1] < (L < 256 * gt.n ? 0.85 : 0.975) * c[0] ? kBwdQuerySplits : 1;

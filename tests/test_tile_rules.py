@@ -43,6 +43,9 @@ SMALL = [
     (4, 128, "teacher_forcing", 1311, 1311, 3, [142.7, 69.31, 77.45], [317.32, 161.51, 171.24], [367.85, 262.32, 266.48, 308.81]),
     (6, 64, "block_causal", 316, 316, 5, [32.37, 25.76, 16.94], [61.98, 40.35, 26.35], [76.82, 63.96, 53.86, 64.11]),
     (5, 64, "teacher_forcing", 843, 843, 2, [62.07, 27.25, 22.67], [108.08, 43.58, 36.28], [136.57, 88.34, 85.03, 111.3]),
+    (12, 64, "teacher_forcing", 383, 696, 3, [65.84, 41.0, 43.35], [102.88, 64.3, 66.4], [141.87, 113.62, 115.51, 135.0]),
+    (16, 128, "teacher_forcing", 98, 98, 12, [46.37, 41.76, 43.13], [97.69, 73.74, 75.76], [132.74, 120.82, 123.04, 120.6]),
+    (5, 128, "teacher_forcing", 2319, 2319, 2, [208.82, 123.62, 135.76], [432.38, 289.91, 295.74], [482.04, 376.45, 378.46, 469.38]),
     (3, 64, "full", 8119, 8119, 1, [133.22, 98.95, 107.2], [269.93, 171.64, 200.41], [296.14, 240.73, 249.47, 316.08]),
 ]
 KIND = {"full": 0, "block_causal": 1, "teacher_forcing": 2}
