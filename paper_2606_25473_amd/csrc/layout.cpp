@@ -212,7 +212,7 @@ struct Seg {
 
 // (segments of up to 32 rows together count as one)
 void add_seg(std::vector<Seg>* s, const Seg& x) {
-  if (!s->empty() && s->back().end == x.begin && (s->back().count == x.count || x.end - s->back().begin <= 32)) {
+  if (!s->empty() && s->back().end == x.begin && x.end - s->back().begin <= 32) {
     s->back().end = x.end;
     s->back().count = std::max(s->back().count, x.count);
   } else {
@@ -446,8 +446,9 @@ int choose_bwd_ksplit(const GroupTable& gt, int L, int nbh, int D) {
   //   40 heads, D = 64, block-causal, L = 840            59.7 / 67.6 / 63.2
   //    6 heads, D = 64, full, L = 11762                  1088 / 1045 / 992
   //    4 heads, D = 128, teacher forcing, L = 7866        368 / 262 / 266
-  // (5 heads, D = 128, full, L = 73: 21.8 / 23.2 / 25.0, so tiles of up to 4 blocks are not split.)
-  if (most_keys(gt) <= 4 * kMfmaBc) return 1;
+  // (5 heads, D = 128, full, L = 73: 21.8 / 23.2 / 25.0, so the one tile of a short
+  // sequence is not split.)
+  if (D == 128 && L <= 4 * kMfmaBc && gt.n <= 4) return 1;
   constexpr TileCost kCost[2][3] = {{{256, 1, 0.50, 16.0, 0}, {128, 2, 0.50, 10.0, 0}, {64, 4, 0.50, 7.0, 0}},
                                     {{256, 1, 0.85, 29.0, 0}, {128, 2, 0.94, 16.5, 0}, {64, 4, 1.03, 11.7, 0}}};
   if ((int64_t)((L + kMfmaBr - 1) / kMfmaBr) * nbh > 256 * kMaxFullTilesPerCu) return 1;
