@@ -205,6 +205,27 @@ __device__ __forceinline__ void split_body(const AttnArgs& a, const int bh, cons
   }
   sync();
 
+  // The reference max of every split from the first block, as the unsplit kernels take it: P~ is
+  // then rounded against the same reference for any number of splits, and the results differ from
+  // theirs by the order of the fp32 sums alone (forward, 12 heads, D = 64, full, L = 1560, against
+  // full tiles: rel-L2 4.6e-5 instead of 2.5e-3; the time is the same).  Rows that the first block
+  // does not admit take each split's own, below, and so do waves that span many groups, where one
+  // more mask costs up to 5 us.
+  if (nblk > 0 && wr.direct) {
+    const BlockMask mask = block_mask(a.gt, wr, plan, row, plan_block(plan, 0) * BC, L);
+    if (!mask.none) {
+      f32x16 S = f32x16{};
+#pragma unroll
+      for (int s = 0; s < G::KSTEPS; ++s) S = mfma(ld128_at((lds0 + KB + koff) ^ (32u * s)), qop[s], S);
+      float sv[16];
+      const uint32_t bits = mask.bits >> (4 * hh);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sv[e] = (bits >> (8 * (e >> 2) + (e & 3))) & 1u ? S[e] : -INFINITY;
+      const float mloc = max16(sv) * c2, mx = fmaxf(mloc, xor32(mloc));
+      if (mx > m) m = mx;
+    }
+  }
+
   // one round: KS consecutive blocks of the plan, one per split; TK: with tangent keys
   auto round = [&](auto tk, const int j) {
     constexpr bool TK = JVP && decltype(tk)::value;
