@@ -345,7 +345,8 @@ def main():
                       "min": round(min(per), 4)},
         "unmasked_pairs_per_head": pairs,
         # pairs the bf16 JVP kernel's 256-row tile plans evaluate, masked lanes included (the
-        # other kernels tile differently: not reported for them)
+        # other kernels tile differently: not reported for them; every bf16 workload here takes
+        # the full-size tiles)
         "computed_over_unmasked": round(computed / pairs, 4) if w.dtype == "bf16" and mode == "jvp" else None,
         # every output of the last timed launch equals the first launch's bit for bit
         "deterministic": deterministic,

@@ -32,10 +32,15 @@
  * - Alignment: every [B, H, L, D] tensor pointer (inputs, tangents, O, dO, gO, gQ, gK,
  *   gV) must be 16-byte aligned, LSE and Delta 4-byte aligned; otherwise
  *   ATTN_ERR_INVALID.
- * - Sizes: B, H, L >= 1, B * H <= 2^20, ceil(L / 128) * B * H <= 2^31 - 1 (work-groups
- *   of one launch); the kernels address a head with 32-bit byte offsets, so bf16 inputs
+ * - Sizes: B, H, L >= 1, B * H <= 2^20, ceil(L / 128) * B * H <= 2^31 - 1 (tiles of
+ *   128 rows in one launch); the kernels address a head with 32-bit byte offsets, so bf16 inputs
  *   need L * D <= 2^31 and fp32 inputs L * D <= 2^30.  Larger sizes are
  *   ATTN_ERR_INVALID.
+ * - Results are deterministic: the same call gives the same bits.  The size of the tiles
+ *   depends on the mask, L, D and B * H, and in bf16 the order of a row's fp32 sums on it: a
+ *   head's bf16 results next to few and to many other heads differ where those sums lie on
+ *   either side of a rounding boundary (relative L2 of 1e-4; up to 2e-3 under masks with
+ *   chunks of a few dozen tokens).  In fp32 a head's bits do not depend on B * H.
  * - Return codes: ATTN_OK, or ATTN_ERR_INVALID (bad pointer, size or layout),
  *   ATTN_ERR_UNSUPPORTED (dtype / head_dim not built), ATTN_ERR_HIP (a HIP
  *   launch error).  All argument and layout validation happens before any HIP
@@ -55,7 +60,10 @@ extern "C" {
 
 /* element types of Q, K, V, dQ, dK, dV, O, dO */
 enum {
-  ATTN_DTYPE_F32 = 0,  /* fp32 in, fp32 math (fp32 matrix cores), fp32 out; D in {64, 128} */
+  ATTN_DTYPE_F32 = 0,  /* fp32 in and out; products from three bf16 parts of each operand (whole 24-bit
+                          operands, below 2^-24 of a product left out) on the bf16 matrix cores, with
+                          fp32 accumulation, and on fp32 matrix instructions where that is not
+                          finite; D in {64, 128} */
   ATTN_DTYPE_BF16 = 1  /* bf16 in, bf16 MFMA with fp32 accumulation, bf16 out; D in {64, 128} */
 };
 
@@ -176,9 +184,13 @@ int attn_bwd(int dtype, int B, int H, int L, int D,
              const float* LSE, const attn_chunk_layout* layout, float softmax_scale,
              void* gQ, void* gK, void* gV, float* Delta, void* stream);
 
+/* The host-only queries below describe the full-size tiles of the bf16 kernels.  Launches
+ * that would leave compute units idle with them take smaller tiles, cut at the bounds of the
+ * query groups; these functions are not given B * H and do not describe those. */
+
 /* Host only.  Query-block plan of key tile `ktile` of the backward's key-tile pass
  * (keys [ktile*K, ktile*K + K) with K = 128, query blocks of 64 rows) as the bf16
- * kernel executes it: the visited query-block indices in visiting order go to
+ * kernel executes it with full-size tiles: the visited query-block indices in visiting order go to
  * blocks[], and full[i] = 1 if every query of block i admits every key of the tile
  * (no per-element mask applied), else 0.  Returns the number of visited blocks, or
  * -1 on an invalid layout, tile index or a too-small buffer (capacity `cap`). */
@@ -190,8 +202,8 @@ int attn_key_tile_plan(const attn_chunk_layout* layout, int L, int ktile, int32_
  * rather than -inf).  Returns -1 (and sets the error message) for an invalid layout. */
 int64_t attn_count_unmasked_pairs(const attn_chunk_layout* layout, int L);
 
-/* Host only.  Number of (query, key) pairs the bf16 kernel actually evaluates
- * for this layout, for one (batch, head): whole key blocks of the tile plans,
+/* Host only.  Number of (query, key) pairs the bf16 JVP evaluates with full-size
+ * tiles for this layout, for one (batch, head): whole key blocks of the tile plans,
  * including the masked lanes of partial blocks (the key/value tiles streamed by
  * Algorithm 1's inner loop, paper App. B, under this library's tiling).  Returns -1
  * on an invalid layout or head_dim. */
@@ -208,12 +220,12 @@ int attn_query_groups(const attn_chunk_layout* layout, int L, int32_t* bounds, i
                       int32_t* ranges, int max_groups, int max_ranges);
 
 /* Host only.  Shape of the work decomposition of the bf16 JVP kernels: query rows
- * per work-group tile and keys per streamed key block (the forward-only kernel takes
- * tiles of half as many rows). */
+ * per full-size work-group tile and keys per streamed key block (the forward-only kernel
+ * takes full-size tiles of half as many rows). */
 void attn_tile_shape(int* rows_per_tile, int* keys_per_block);
 
 /* Host only.  Key-block plan of query tile `qtile` (rows [qtile*R, qtile*R + R)
- * with R from attn_tile_shape) as the bf16 kernels execute it: the visited key
+ * with R from attn_tile_shape) as the bf16 JVP executes it with full-size tiles: the visited key
  * block indices in visiting order go to blocks[], and full[i] = 1 if block i is
  * admissible for every row of the tile (no per-row mask applied), else 0.
  * Returns the number of visited blocks, or -1 on an invalid layout, tile index
@@ -221,8 +233,8 @@ void attn_tile_shape(int* rows_per_tile, int* keys_per_block);
 int attn_tile_plan(const attn_chunk_layout* layout, int L, int qtile,
                    int32_t* blocks, int32_t* full, int cap);
 
-/* Host only.  Order in which the bf16 kernels' work-groups of one (batch, head)
- * take query tiles: order[t] = query tile of the t-th work-group (a permutation
+/* Host only.  Order in which the work-groups of one (batch, head) of the bf16 JVP take
+ * full-size query tiles: order[t] = query tile of the t-th work-group (a permutation
  * of 0 .. ceil(L / R) - 1, heaviest tiles first where the layout makes the
  * per-tile work predictable).  zero_clean != 0 gives the order of
  * attn_jvp_fwd_zero_clean, else that of attn_jvp_fwd / attn_fwd.  Returns the

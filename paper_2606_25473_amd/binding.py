@@ -299,7 +299,7 @@ def count_unmasked_pairs(kind, offsets, L):
 
 
 def count_computed_pairs(kind, offsets, L, D=128):
-    """Pairs the bf16 kernel evaluates per (batch, head), masked lanes included."""
+    """Pairs the bf16 JVP evaluates per (batch, head) with full-size tiles, masked lanes included."""
     n = load_library().attn_count_computed_pairs(ctypes.byref(make_layout(kind, offsets)), int(L), int(D))
     if n < 0:
         raise AttnError(1, last_error())
@@ -313,14 +313,14 @@ def query_groups(kind, offsets, L):
 
 
 def tile_shape():
-    """(query rows per tile, keys per block) of the bf16 kernels."""
+    """(query rows per full-size tile, keys per block) of the bf16 JVP."""
     r, k = _i(), _i()
     load_library().attn_tile_shape(ctypes.byref(r), ctypes.byref(k))
     return r.value, k.value
 
 
 def tile_order(kind, offsets, L, zero_clean=False):
-    """Query tile taken by the t-th work-group of a (batch, head), for t = 0, 1, ..."""
+    """Full-size query tile taken by the t-th work-group of a (batch, head), for t = 0, 1, ..."""
     R, _ = tile_shape()
     cap = (int(L) + R - 1) // R
     buf = (ctypes.c_int32 * max(cap, 1))()
@@ -332,7 +332,7 @@ def tile_order(kind, offsets, L, zero_clean=False):
 
 
 def key_tile_plan(kind, offsets, L, ktile):
-    """[(query_block, is_full), ...] visited by key tile ``ktile`` of the bf16 backward
+    """[(query_block, is_full), ...] visited by full-size key tile ``ktile`` of the bf16 backward
     (128 keys per tile, 64-row query blocks)."""
     cap = (int(L) + 63) // 64 + 8
     blocks = (ctypes.c_int32 * cap)()
@@ -345,7 +345,7 @@ def key_tile_plan(kind, offsets, L, ktile):
 
 
 def tile_plan(kind, offsets, L, qtile):
-    """[(key_block, is_full), ...] visited by query tile ``qtile`` of the bf16 kernels."""
+    """[(key_block, is_full), ...] visited by full-size query tile ``qtile`` of the bf16 JVP."""
     cap = (int(L) + 31) // 32 + 8
     blocks = (ctypes.c_int32 * cap)()
     full = (ctypes.c_int32 * cap)()

@@ -20,7 +20,7 @@
 // (the scores S and gP are computed in both), against 10 D for a single pass that would
 // need atomic gQ updates.
 //
-// The fp32 entry point runs the same two passes on fp32 matrix cores (attn_f32.hip).
+// The fp32 entry point runs the same two passes with three-part products (attn_f32.hip).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>

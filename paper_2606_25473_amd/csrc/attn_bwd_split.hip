@@ -10,7 +10,7 @@
 // Both stage one block per split in LDS, in two stages (the next round's blocks stream in
 // while a round is computed, one barrier per round).  Per block and wave the matrix work and
 // the operand reads are those of attn_bwd.hip; the L2 traffic grows with the splits, so full
-// launches keep the larger tiles (choose_ksplit, choose_qsplit in layout.cpp).
+// launches keep the larger tiles (choose_bwd_ksplit, choose_qsplit in layout.cpp).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>

@@ -12,7 +12,7 @@
 //
 // What bounds it: per key block and wave the matrix work is that of attn_mfma.hip, but a
 // block staged in LDS serves RG waves instead of 8, so the traffic from L2 grows 8 / RG
-// times; that is why full launches keep the larger tiles (choose_split in layout.cpp).
+// times; that is why full launches keep the larger tiles (choose_ksplit in layout.cpp).
 //
 // LDS holds one key block per split and stage, in two stages where they fit (the next round's
 // blocks stream in while a round is computed, one barrier per round).  The D = 128 JVP with
@@ -377,7 +377,8 @@ __device__ __forceinline__ void split_body(const AttnArgs& a, const int bh, cons
 
   // ---- merge the KS partial results of each row (no load is in flight: the last round
   // issued none).  With M the largest reference max, split s enters with weight
-  // 2^(m_s - M); a split that saw no key has m = -inf, l = 0 and weight 0.
+  // 2^(m_s - M); a split that saw no key of the row has l = 0 (and where the first block gave it
+  // no reference either, m = -inf and weight 0).
   float* const st = (float*)(lds + G::XCHG);
   const float lt = lsum + xor32(lsum);
   const float rt = JVP ? rsum + xor32(rsum) : 0.f;

@@ -18,7 +18,7 @@ bool build_groups(const attn_chunk_layout* layout, int L, GroupTable* gt, std::s
 // Admissible (query, key) pairs of the mask, one (batch, head).
 int64_t count_pairs(const GroupTable& gt);
 
-// Pairs evaluated by a kernel with br-row query tiles and bc-key blocks.
+// Pairs evaluated by a kernel with (uncut) br-row query tiles and bc-key blocks.
 int64_t count_computed_pairs(const GroupTable& gt, int L, int br, int bc);
 
 // Key splits per query tile of the bf16 forward and JVP kernels (1: none, 128- and 256-row

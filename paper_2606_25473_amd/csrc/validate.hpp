@@ -21,7 +21,8 @@ int prepare(Pass pass, int dtype, int B, int H, int L, int D, const void* Q, con
             const void* dQ, const void* dK, const void* dV, const attn_chunk_layout* layout,
             float softmax_scale, void* O, void* dO, float* LSE, AttnArgs* args);
 
-// Validation of attn_bwd: `qa` gets the query-group table, `ka` the key-group table.
+// Validation of attn_bwd: `qa` are the query-tile pass's arguments, `ka` the key-tile pass's (both
+// hold the query-group table).
 int prepare_bwd(int dtype, int B, int H, int L, int D, const void* Q, const void* K, const void* V,
                 const void* O, const void* gO, const float* LSE, const attn_chunk_layout* layout,
                 float softmax_scale, void* gQ, void* gK, void* gV, float* Delta, BwdArgs* qa, BwdArgs* ka);

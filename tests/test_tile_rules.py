@@ -14,6 +14,8 @@ import subprocess
 
 import pytest
 
+from paper_2606_25473_amd.workloads import WORKLOADS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # launches that fill the chip with full tiles, or nearly, and tiles of a few blocks
@@ -48,6 +50,9 @@ SMALL = [
     (5, 128, "teacher_forcing", 2319, 2319, 2, [208.82, 123.62, 135.76], [432.38, 289.91, 295.74], [482.04, 376.45, 378.46, 469.38]),
     (3, 64, "full", 8119, 8119, 1, [133.22, 98.95, 107.2], [269.93, 171.64, 200.41], [296.14, 240.73, 249.47, 316.08]),
 ]
+# the bf16 workloads that bench.py runs: all full tiles (its ratio of computed pairs counts those)
+BENCH = [(w.B * w.H, w.D, w.kind, w.offsets[1] if w.offsets else w.L, w.offsets[1] if w.offsets else w.L,
+          max(1, len(w.offsets) - 1)) for w in WORKLOADS.values() if w.dtype == "bf16"]
 KIND = {"full": 0, "block_causal": 1, "teacher_forcing": 2}
 
 
@@ -56,7 +61,7 @@ def chosen(tmp_path_factory):
     """row -> (key splits of the forward and JVP, of the query-tile pass, query splits)"""
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
-    rows, calls = FULL + SMALL, []
+    rows, calls = FULL + SMALL + BENCH, []
     for nbh, D, kind, first, chunk, n, *_ in rows:
         o = [0] + [first + i * chunk for i in range(n)]
         L = o[-1] * (2 if kind == "teacher_forcing" else 1)
@@ -96,3 +101,9 @@ def test_no_launch_is_slower_than_with_full_tiles(row, chosen):
 def test_small_launches_are_near_the_best_tiling(chosen):
     logs = [math.log(got / best) for r in SMALL for got, best in _ratios(r, *chosen[id(r)])]
     assert math.exp(sum(logs) / len(logs)) <= 1.10
+
+
+def test_bench_workloads_take_full_tiles(chosen):
+    assert len(BENCH) >= 4
+    for row in BENCH:
+        assert chosen[id(row)] == (1, 1, 1), row
