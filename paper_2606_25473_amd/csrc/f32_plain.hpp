@@ -1,7 +1,7 @@
 // f32_plain.hpp -- fp32 masked attention on fp32 matrix instructions: the bodies that the kernels
-// of attn_f32.hip run for a tile whose result is not finite (infinities or NaN among the
-// operands, or values within a rounding of the largest fp32 number, which have no sum of three
-// bf16 parts).  Device code only.
+// of attn_f32.hip run for a tile whose result is not finite there (infinities or NaN among the
+// operands, or operands, products or sums beyond the range of the scaled parts).  Such a tile is
+// walked twice.  Device code only.
 //
 // One work-group of NW waves owns a query tile of 16 NW rows, 16 per wave,
 // and streams the key blocks of its plan (schedule.hpp) through LDS, 32 keys at a time, in
