@@ -15,10 +15,10 @@ and the backward through the adjoint identity with the JVP over the whole head, 
 the sampled rows against the oracle on the same gathered problems.
 
 The identity's fp32 bound is wider than the element-wise one.  The first 256 keys are
-admitted by every row, so their gK and gV are sums over all L = 2^23 rows: 2^21 dependent
-fp32 additions per output element (four rows per matrix instruction).  For the random-signed
-terms here, the rounding error of such a sum grows like sqrt(2^21) 2^-24 = 8.7e-5 relative,
-and these keys carry a large share of <gK, dK> + <gV, dV>.  The bound is 5e-4, a little over
+admitted by every row, so their gK and gV are sums over all L = 2^23 rows: 2^18 dependent
+fp32 additions per output element (one for each block of 32 rows).  For the random-signed
+terms here, the rounding error of such a sum grows like sqrt(2^18) 2^-24 = 3.1e-5 relative,
+and these keys carry a large share of <gK, dK> + <gV, dV>.  The bound is 1.6e-4, a little over
 five times that estimate; every element-wise comparison keeps the fp32 bar of 1e-4.
 """
 import sys
@@ -36,7 +36,7 @@ pytestmark = pytest.mark.gpu
 D, W, G = 128, 256, 64
 # dtype: sequence length (the largest with L * D within the 32-bit byte offsets), tolerance
 CASES = {"bf16": (1 << 24, 1e-2), "f32": (1 << 23, 1e-4)}
-ADJOINT_TOL = {"bf16": 1e-2, "f32": 5e-4}
+ADJOINT_TOL = {"bf16": 1e-2, "f32": 1.6e-4}
 
 
 def _groups(L):
